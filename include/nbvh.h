@@ -162,7 +162,8 @@ typedef struct {
  * [fan_out][fan_in] (no biases); each block starts on a 64-element
  * boundary and the gaps are zero (nbvh_param_layout gives the offsets).
  * params_lp is the BF16 shadow of params in
- * the same layout (written by nbvh_sync_shadow and by every Adam step);
+ * the same layout (written by nbvh_sync_shadow and by every Adam step; BF16
+ * queries and forward passes read table and weights as they find them there);
  * it may be NULL only if precision is FP32. grad accumulates dL/dparams
  * (times loss_scale) and is cleared by each optimiser step. state_dev is
  * nbvh_state_bytes() bytes. Every buffer must be 16-byte aligned
@@ -175,7 +176,7 @@ typedef struct {
   float* grad_dev;
   void* state_dev;
   void* aux_dev; /* nbvh_aux_bytes(cfg) bytes: weight copies in the kernels' own order (back-propagation,
-                    BF16 forward), then the FP8 weights and scales */
+                    scratch of BF16 queries), then the FP8 weights and scales */
 } nbvh_params;
 
 /* Host copy of the device state block. */
@@ -246,9 +247,10 @@ nbvh_status nbvh_param_count(const nbvh_config* cfg, uint64_t* n_table, uint64_t
  * mlp_hidden + 3 entries. */
 nbvh_status nbvh_param_layout(const nbvh_config* cfg, uint64_t* offsets);
 
-/* Bytes of the auxiliary buffer: FP32 and BF16 weight copies in the kernels'
- * own order (rewritten by nbvh_sync_shadow and every optimiser step), then E4M3
- * weights and per-layer scales (written by nbvh_calibrate_fp8). */
+/* Bytes of the auxiliary buffer: transposed FP32 and BF16 weight copies in the
+ * kernels' own order (rewritten by nbvh_sync_shadow and every optimiser step),
+ * BF16 ones that every BF16 query rewrites from params_lp, then E4M3 weights
+ * and per-layer scales (written by nbvh_calibrate_fp8). */
 size_t nbvh_aux_bytes(const nbvh_config* cfg);
 
 /* Bytes of the node buffer nbvh_build writes for n_leaves leaves:

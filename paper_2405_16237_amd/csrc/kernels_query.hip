@@ -241,7 +241,7 @@ __device__ inline void query_eval_loop(const DevCfg& c, const QueryJob& J, unsig
       if (c1 < s_end[lane]) nxt = J.segs[c1];
     }
     // the first weights travel while the table is gathered
-    Group<AT> g = first_group(forward_layer<AT>(c, (const AT*)J.W, 0));
+    Group<AT> g = first_group(forward_layer<kOrderedQuery<AT>>(c, (const AT*)J.W, 0));
     const float qscale = sizeof(AT) == 1 ? J.scales[kMaxLayers] : 1.0f;
     if (!kTail || rows > 32)
       encode_tile<AT, F, LP, NW, U, PR>(c, J.table, sA, sB, pos, s_valid, act0, ld0, qscale, ltab, J.lds_levels);
@@ -260,10 +260,10 @@ __device__ inline void query_eval_loop(const DevCfg& c, const QueryJob& J, unsig
       }
     }
     if (!kTail || rows > 32)
-      mlp_forward_tile<kQM, NW, AT>(c, (const AT*)J.W, J.scales, act0, ld0, act1, ld1, z, kOutPad, g);
+      mlp_forward_tile<kQM, NW, kOrderedQuery<AT>, AT>(c, (const AT*)J.W, J.scales, act0, ld0, act1, ld1, z, kOutPad, g);
     else if constexpr (kTail) {
-      if (rows > 16) mlp_forward_tile<32, NW, AT>(c, (const AT*)J.W, J.scales, act0, ld0, act1, ld1, z, kOutPad, g);
-      else mlp_forward_tile<16, NW, AT>(c, (const AT*)J.W, J.scales, act0, ld0, act1, ld1, z, kOutPad, g);
+      if (rows > 16) mlp_forward_tile<32, NW, kOrderedQuery<AT>, AT>(c, (const AT*)J.W, J.scales, act0, ld0, act1, ld1, z, kOutPad, g);
+      else mlp_forward_tile<16, NW, kOrderedQuery<AT>, AT>(c, (const AT*)J.W, J.scales, act0, ld0, act1, ld1, z, kOutPad, g);
     }
 
     if (wave == 0 && s_valid[lane]) {
@@ -394,12 +394,12 @@ __device__ inline void query_direct(const DevCfg& c, const QueryJob& J, unsigned
       sA[threadIdx.x] = make_float4(ra.x, ra.y, ra.z, in ? -sg.t1 : sg.t0);
       sB[threadIdx.x] = in ? make_float4(-rb.x, -rb.y, -rb.z, -sg.t0) : make_float4(rb.x, rb.y, rb.z, sg.t1);
     }
-    Group<AT> g = first_group(forward_layer<AT>(c, (const AT*)J.W, 0));
+    Group<AT> g = first_group(forward_layer<kOrderedQuery<AT>>(c, (const AT*)J.W, 0));
     __syncthreads();
     encode_rows<AT, F, LP, NW, kDirectRows>(c, J.table, sA, sB, kDirectRows, act0, ld0,
                                             sizeof(AT) == 1 ? J.scales[kMaxLayers] : 1.0f);
     __syncthreads();
-    mlp_forward_tile<kDirectRows, NW, AT>(c, (const AT*)J.W, J.scales, act0, ld0, act1, ld1, z, kOutPad, g);
+    mlp_forward_tile<kDirectRows, NW, kOrderedQuery<AT>, AT>(c, (const AT*)J.W, J.scales, act0, ld0, act1, ld1, z, kOutPad, g);
     if (wave == 0) {
       while (more && cur - base < (uint32_t)kDirectRows) {
         const int m = (int)(cur - base);
@@ -481,7 +481,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
 // caller-given segment queue). Also clears the ray counter of the eval kernel.
 __global__ __launch_bounds__(256) void k_active_rays(const uint32_t* __restrict__ offsets, uint32_t n_rays,
                                                      nbvh_hit* __restrict__ hits, uint32_t* __restrict__ active,
-                                                     uint32_t* __restrict__ n_active) {
+                                                     uint32_t* __restrict__ n_active, DevCfg c, WeightCopy wc) {
+  if (blockIdx.x >= ray_blocks(n_rays)) return order_weights(c, wc, blockIdx.x - ray_blocks(n_rays));
   const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
   const bool valid = r < n_rays;
   const bool want = valid && offsets[r + 1] > offsets[r];
@@ -504,7 +505,9 @@ __global__ __launch_bounds__(256) void k_active_rays(const uint32_t* __restrict_
 nbvh_status launch_active_rays(const LaunchCtx& L, const uint32_t* offsets, uint32_t n_rays, nbvh_hit* hits,
                                uint32_t* active, uint32_t* misc) {
   k_zero_u32<<<1, 64, 0, L.stream>>>(misc, 1 + kXcds);
-  if (n_rays) k_active_rays<<<(n_rays + 255) / 256, 256, 0, L.stream>>>(offsets, n_rays, hits, active, misc);
+  const WeightCopy wc = weight_copy(L);
+  if (n_rays)
+    k_active_rays<<<ray_blocks(n_rays) + wc.blocks, 256, 0, L.stream>>>(offsets, n_rays, hits, active, misc, L.cfg, wc);
   return check_launch("active_rays");
 }
 
@@ -533,10 +536,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     s_valid[threadIdx.x] = v ? 1 : 0;
   }
   __syncthreads();
-  Group<AT> g = first_group(forward_layer<AT>(c, (const AT*)W, 0));
+  Group<AT> g = first_group(forward_layer<kOrderedForward<AT>>(c, (const AT*)W, 0));
   encode_tile<AT, F, LP, kQWaves>(c, table, sA, sB, pos, s_valid, act0, ld0, sizeof(AT) == 1 ? scales[kMaxLayers] : 1.0f);
   __syncthreads();
-  mlp_forward_tile<kQM, kQWaves, AT>(c, (const AT*)W, scales, act0, ld0, act1, ld1, z, kOutPad, g);
+  mlp_forward_tile<kQM, kQWaves, kOrderedForward<AT>, AT>(c, (const AT*)W, scales, act0, ld0, act1, ld1, z, kOutPad, g);
   for (int e = threadIdx.x; e < kQM * c.n_out; e += blockDim.x) {
     const int m = e / c.n_out, o = e - m * c.n_out;
     if (base + m < n) zout[(size_t)(base + m) * c.n_out + o] = z[m * kOutPad + o];
@@ -588,10 +591,11 @@ static int query_per_cu(const LaunchCtx& L, size_t lds) {
   return per_cu;
 }
 
-// the weights forward_layer reads: fragment-ordered copies, FP32 the parameters
-static const void* forward_weights(const LaunchCtx& L) {
+// the weights forward_layer reads, of a query or of the other calls
+static const void* mlp_weights(const LaunchCtx& L, bool query) {
   if (L.fp8) return (const char*)L.aux + fp8_weights_off(L.cfg);
-  return L.precision == NBVH_FP32 ? (const void*)L.params : (const void*)((const char*)L.aux + wf16_off(L.cfg));
+  if (L.precision == NBVH_FP32) return L.params;
+  return query ? (const void*)((const char*)L.aux + wf16_off(L.cfg)) : (const void*)L.params_lp;
 }
 
 // merge per-object hit records: closest t, ties to the lower object index
@@ -646,7 +650,7 @@ nbvh_status launch_query_eval_batch(const LaunchCtx* Ls, int n_obj, const DevCfg
   for (int k = 0; k < n_obj; ++k) {
     const LaunchCtx& Lk = Ls[k];
     QueryJob& J = jobs[k];
-    J.W = forward_weights(Lk);
+    J.W = mlp_weights(Lk, true);
     J.scales = (const float*)((const char*)Lk.aux + fp8_scales_off(Lk.cfg));
     J.table = (Lk.precision != NBVH_FP32) ? (const void*)Lk.params_lp : (const void*)Lk.params;
     J.rays = rays;
@@ -698,7 +702,7 @@ static nbvh_status query_eval_t(const LaunchCtx& L, const nbvh_ray* rays, const 
   const uint32_t need = (n_rays_bound + kQM - 1) / kQM;
   if (need < grid) grid = need > 0 ? need : 1;
   QueryJob J;
-  J.W = forward_weights(L);
+  J.W = mlp_weights(L, true);
   J.scales = (const float*)((const char*)L.aux + fp8_scales_off(c));
   J.table = LP ? (const void*)L.params_lp : (const void*)L.params;
   J.rays = rays;
@@ -750,7 +754,7 @@ static nbvh_status forward_t(const LaunchCtx& L, const nbvh_probe* probes, uint3
   if (lds_fits(lds, "the forward pass") != NBVH_OK) return NBVH_ERR_UNSUPPORTED;
   auto kern = k_forward<AT, F, LP>;
   set_lds(kern, lds);
-  const void* W = forward_weights(L);
+  const void* W = mlp_weights(L, false);
   const float* scales = (const float*)((const char*)L.aux + fp8_scales_off(c));
   const void* table = LP ? (const void*)L.params_lp : (const void*)L.params;
   if (n == 0) return NBVH_OK;
@@ -846,8 +850,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
   m0 = wave_max(m0);
   if ((threadIdx.x & 63) == 0) amax_lds(s_amax, m0);
-  Group<float> g = first_group(forward_layer<float>(c, W, 0));
-  mlp_forward_tile_keep<kQM, kQWaves, float>(c, W, nullptr, act0, ld0, act1, ld1, z, kOutPad, g,
+  Group<float> g = first_group(forward_layer<false>(c, W, 0));
+  mlp_forward_tile_keep<kQM, kQWaves, false, float>(c, W, nullptr, act0, ld0, act1, ld1, z, kOutPad, g,
                                              [&](int k, int m, int, f32x4 v) {
                                                if (s_valid[m]) {
                                                  const float mx = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));

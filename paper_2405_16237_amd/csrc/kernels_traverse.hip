@@ -401,8 +401,9 @@ __global__ __launch_bounds__(256) void k_traverse_count(const Node* __restrict__
                                                         uint32_t n_rays, uint32_t* __restrict__ counts,
                                                         nbvh_hit* __restrict__ hits, float* __restrict__ staging,
                                                         int mode, const uint32_t* __restrict__ perm, uint32_t n_nodes,
-                                                        uint32_t stack_words) {
+                                                        uint32_t stack_words, DevCfg c, WeightCopy wc) {
   extern __shared__ __align__(16) int32_t s_stack[];  // the stacks, then the tree
+  if (blockIdx.x >= ray_blocks(n_rays)) return order_weights(c, wc, blockIdx.x - ray_blocks(n_rays));
   const Node* tree = copy_tree<TREE>(nodes, n_nodes, s_stack + stack_words);
   // thread i takes ray perm[i] (ray i without a ray order); its staged run
   // is column i, so a wave's staging stores stay coalesced
@@ -834,7 +835,9 @@ __global__ __launch_bounds__(256) void k_traverse_one(const Node* __restrict__ n
                                                       uint32_t* __restrict__ offsets,
                                                       uint32_t* __restrict__ pos, uint32_t* __restrict__ active,
                                                       uint32_t* __restrict__ n_active, nbvh_segment* __restrict__ segs,
-                                                      uint64_t capacity, DevState* __restrict__ state) {
+                                                      uint64_t capacity, DevState* __restrict__ state, DevCfg c,
+                                                      WeightCopy wc) {
+  if (blockIdx.x > 0) return order_weights(c, wc, blockIdx.x - 1);
   // the stacks, the staged runs (a record read back for an insertion takes 1 to
   // 2 us from global memory), then the tree
   extern __shared__ __align__(16) int32_t s_stack[];
@@ -1403,7 +1406,8 @@ nbvh_status launch_traverse(const LaunchCtx& L, const nbvh_ray* rays, uint32_t n
   if (active && (!n_active || !segs || !scratch_pos || !scratch_sums2))
     return set_error("active-ray list without its buffers"), NBVH_ERR_INVALID_ARG;
   ProfScope ps(L.prof, NBVH_K_TRAVERSE, L.stream);
-  const int grid = (int)((n_rays + 255) / 256);
+  const uint32_t grid = ray_blocks(n_rays);
+  const WeightCopy wc = active ? weight_copy(L) : WeightCopy{nullptr, nullptr, 0};  // a query follows
   const uint32_t stack_words = 256u * (uint32_t)(L.stack_depth > 0 ? L.stack_depth : 1);
   const bool in_lds = n_rays <= kTreeRays && L.n_nodes <= kTreeNodes && L.tune.traverse_mode != 1;
   const size_t lds = (size_t)stack_words * 4 + (in_lds ? (size_t)L.n_nodes * sizeof(Node) : 0);
@@ -1412,8 +1416,8 @@ nbvh_status launch_traverse(const LaunchCtx& L, const nbvh_ray* rays, uint32_t n
                                      : (in_lds ? k_traverse_one<false, true> : k_traverse_one<false, false>);
     const size_t one = lds + (size_t)kStage * 3 * 256 * 4;  // at most 48 + 48 + 64 KiB
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)one);
-    kern<<<1, 256, one, L.stream>>>(L.nodes, rays, n_rays, hits, L.tune.traverse_mode, L.n_nodes, stack_words, offsets,
-                                    scratch_pos, active, n_active, segs, capacity, L.state);
+    kern<<<1 + wc.blocks, 256, one, L.stream>>>(L.nodes, rays, n_rays, hits, L.tune.traverse_mode, L.n_nodes, stack_words,
+                                                offsets, scratch_pos, active, n_active, segs, capacity, L.state, L.cfg, wc);
     if (active_order_ws && L.tune.query_order != 0)
       return order_active_list(L, rays, n_rays, active, n_active, L.tune.query_order, active_order_ws);
     return check_launch("traverse");
@@ -1422,8 +1426,9 @@ nbvh_status launch_traverse(const LaunchCtx& L, const nbvh_ray* rays, uint32_t n
     auto kern = L.cfg.inside_reverse ? (in_lds ? k_traverse_count<true, true> : k_traverse_count<true, false>)
                                      : (in_lds ? k_traverse_count<false, true> : k_traverse_count<false, false>);
     if (in_lds) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    kern<<<grid, 256, lds, L.stream>>>(L.nodes, rays, n_rays, scratch_counts, hits, segs ? staging : nullptr,
-                                       L.tune.traverse_mode, order ? order->perm : nullptr, L.n_nodes, stack_words);
+    kern<<<grid + wc.blocks, 256, lds, L.stream>>>(L.nodes, rays, n_rays, scratch_counts, hits, segs ? staging : nullptr,
+                                                   L.tune.traverse_mode, order ? order->perm : nullptr, L.n_nodes,
+                                                   stack_words, L.cfg, wc);
   }
   const uint32_t n_tiles = n_rays > 0 ? (n_rays + kScanTile - 1) / kScanTile : 1;
   const int scanned = n_tiles > kScanDirectTiles ? 1 : 0;

@@ -62,7 +62,7 @@ struct LaunchCtx {
   float* adam_m;
   float* adam_v;
   float* grad;
-  void* aux;  // weight copies in fragment order and FP8 scales (aux_total_bytes)
+  void* aux;  // weight copies and FP8 scales (aux_total_bytes)
   bool fp8;   // queries and forward run the MLP in FP8 (weights and scales in aux)
   uint32_t n_nodes;
   int stack_depth;  // inner levels of the N-BVH: entries of a traversal stack
@@ -79,6 +79,36 @@ void set_error(const char* fmt, ...);
 
 __global__ void k_zero_u32(uint32_t* p, uint32_t n);
 __global__ void k_zero_f32(float* p, uint64_t n);
+
+// BF16 queries read the MLP weights in fragment order. The copies are made in
+// every query, as the caller may have written the shadow since the last one, by
+// workgroups of its traversal beside those of the rays: a launch of its own
+// would take 3 us. Queries of one context on several streams write the same
+// values.
+struct WeightCopy {
+  const void* src;  // the BF16 shadow of the parameters
+  void* dst;        // the copies
+  uint32_t blocks;  // workgroups of 256 threads, 16 bytes a thread (0: nothing to copy)
+};
+
+inline WeightCopy weight_copy(const LaunchCtx& L) {
+  if (L.precision != NBVH_BF16 || L.fp8) return WeightCopy{nullptr, nullptr, 0};
+  return WeightCopy{L.params_lp, (char*)L.aux + wf16_off(L.cfg), (uint32_t)((L.cfg.n_wf / 8 + 255) / 256)};
+}
+
+// workgroups of 256 rays
+__host__ __device__ inline uint32_t ray_blocks(uint32_t n_rays) { return (uint32_t)(((uint64_t)n_rays + 255) / 256); }
+
+__device__ inline void order_weights(const DevCfg& c, const WeightCopy& wc, uint32_t block) {
+  const uint64_t e = ((uint64_t)block * 256 + threadIdx.x) * 8;  // eight columns of a row: a lane's part of a fragment
+  if (e >= c.n_wf) return;
+  int k = 0;
+  while (k < c.hidden && e >= c.wf_off[k + 1]) ++k;
+  const uint32_t K = (uint32_t)c.fan_in[k], at = (uint32_t)(e - c.wf_off[k]) / 8, lane = at & 63u, frag = at >> 6;
+  const uint32_t n = frag / (K / 32) * 16 + (lane & 15u), col = frag % (K / 32) * 32 + (lane >> 4) * 8;
+  if (n < (uint32_t)c.fan_out[k])  // the last rows of a padded tile hold nothing
+    *(uint4*)((uint16_t*)wc.dst + e) = *(const uint4*)((const uint16_t*)wc.src + c.w_off[k] + (uint64_t)n * K + col);
+}
 
 // A permutation of the rays (launch_ray_order): the traversal's counting pass
 // takes them in perm order; inv[r] is ray r's position in perm.
@@ -99,7 +129,8 @@ nbvh_status launch_ray_order(const LaunchCtx& L, const nbvh_ray* rays, uint32_t 
 // built instead. With `active` (the list of rays with a segment,
 // in ray order; its length goes to *n_active, and the query's eight ray-queue
 // counters after it are cleared), `segs`, scratch_pos
-// (n_rays + 1 words) and scratch_sums2 (like scratch_sums) are required.
+// (n_rays + 1 words) and scratch_sums2 (like scratch_sums) are required, and
+// the query's weight copies are made.
 size_t traverse_staging_bytes(uint64_t n_rays);
 nbvh_status launch_traverse(const LaunchCtx& L, const nbvh_ray* rays, uint32_t n_rays, uint32_t* offsets,
                             nbvh_segment* segs, uint64_t capacity, nbvh_hit* hits, uint32_t* active,

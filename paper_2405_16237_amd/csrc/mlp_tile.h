@@ -2,10 +2,9 @@
 //
 // A layer computes out[m][n] = sum_k act[m][k] * W[n][k] (no bias). It is
 // issued as the transposed product out^T = W x act^T: the A fragment is 16
-// rows of W by 32 (FP32: 16) columns, read from the weight copies in fragment
-// order (or, FP32 forward, from the row-major parameters themselves, which the
-// caller may have edited); the B fragment is the same columns of 16 activation
-// rows, from LDS. The 16x16 accumulator tile of a lane then holds 4 consecutive
+// rows of W by 32 (FP32: 16) columns, read from copies in fragment order or
+// from the row-major parameters themselves (FP32, or their BF16 shadow); the B
+// fragment is the same columns of 16 activation rows, from LDS. The 16x16 accumulator tile of a lane then holds 4 consecutive
 // output features of one row, handed to the epilogue (ReLU + store, mask +
 // store, raw store).
 //
@@ -15,7 +14,12 @@
 // one contiguous kilobyte, and a fragment's registers are loaded again as soon
 // as its products are issued, across column tiles and the layers' barriers.
 // Bounce-ray query, MLP 256-4x256-8: 4.46 -> 3.84 ms; 1920x1080 query, MLP
-// 256-4x128-5: 2.39 -> 2.30 ms.
+// 256-4x128-5: 2.39 -> 2.30 ms. FP32, and BF16 outside queries, read the
+// parameters: the caller may have written them, so a copy has to be made in
+// every call. A query's traversal makes it on the side (10^6 camera rays, these
+// two networks: 940 and 1,111 us with it, 1,092 and 1,205 from the parameters);
+// a forward pass would need a launch more for what it gains (30,000 segments:
+// 114 and 157 us, 118 and 158 from the parameters), a training step gains nothing.
 //
 // BF16: v_mfma_f32_16x16x32_bf16, activations rounded to bf16 between layers.
 // FP8: 16x16x32 E4M3. FP32: v_mfma_f32_16x16x4_f32. FP32 accumulation.
@@ -209,14 +213,18 @@ __device__ inline void store4(AT* dst, f32x4 v) {
   }
 }
 
-// Forward weights of layer k: the copies in fragment order (BF16, E4M3) or the
-// FP32 parameters.
+// What a query's tiles and the other calls' forward tiles read: copies in
+// fragment order (E4M3 from the calibration, a query's BF16 ones made by its
+// traversal, see order_weights) or the parameters and their BF16 shadow.
 template <typename AT>
-constexpr bool kOrderedForward = sizeof(AT) < 4;
+constexpr bool kOrderedQuery = sizeof(AT) < 4;
+template <typename AT>
+constexpr bool kOrderedForward = sizeof(AT) == 1;
 
-template <typename AT>
-__device__ inline LayerW<AT, kOrderedForward<AT>> forward_layer(const DevCfg& c, const AT* base, int k) {
-  return LayerW<AT, kOrderedForward<AT>>{base + (kOrderedForward<AT> ? c.wf_off[k] : c.w_off[k]), c.fan_in[k], c.fan_out[k]};
+// weights of layer k
+template <bool ORDERED, typename AT>
+__device__ inline LayerW<AT, ORDERED> forward_layer(const DevCfg& c, const AT* base, int k) {
+  return LayerW<AT, ORDERED>{base + (ORDERED ? c.wf_off[k] : c.w_off[k]), c.fan_in[k], c.fan_out[k]};
 }
 
 // Full forward of the tile: act0 holds the encoded input [M][n_in]; hidden
@@ -226,7 +234,7 @@ __device__ inline LayerW<AT, kOrderedForward<AT>> forward_layer(const DevCfg& c,
 // quantised with the activation scale sa[0], each hidden output is
 // dequantised, ReLU'd and requantised with sa[k + 1] (scales: sw[kMaxLayers],
 // then sa[kMaxLayers]).
-template <int M, int NWAVES, typename AT, typename Keep>
+template <int M, int NWAVES, bool ORDERED, typename AT, typename Keep>
 __device__ inline void mlp_forward_tile_keep(const DevCfg& c, const AT* Wbase, const float* scales, AT* act0, int ld0,
                                              AT* act1, int ld1, float* z, int ldz, Group<AT>& g, Keep keep) {
   AT* cur = act0;
@@ -235,7 +243,7 @@ __device__ inline void mlp_forward_tile_keep(const DevCfg& c, const AT* Wbase, c
   int ldn = ld1;
   for (int k = 0; k <= c.hidden; ++k) {
     const bool last = (k == c.hidden);
-    const auto w = forward_layer<AT>(c, Wbase, k);
+    const auto w = forward_layer<ORDERED>(c, Wbase, k);
     const float dq = sizeof(AT) == 1 ? 1.0f / (scales[k] * scales[kMaxLayers + k]) : 1.0f;  // 1 / (sw_k * sa_k)
     if (last) {
       gemm_tile<M, NWAVES, AT>(cur, ldc, w, g, [&](int m, int col, f32x4 v) {
@@ -243,7 +251,7 @@ __device__ inline void mlp_forward_tile_keep(const DevCfg& c, const AT* Wbase, c
         lds_store<f32x4>(z + (size_t)m * ldz + col, v);
       });
     } else {
-      const auto wn = forward_layer<AT>(c, Wbase, k + 1);
+      const auto wn = forward_layer<ORDERED>(c, Wbase, k + 1);
       const float qn = sizeof(AT) == 1 ? scales[kMaxLayers + k + 1] : 1.0f;
       gemm_tile<M, NWAVES, AT>(
           cur, ldc, w, g,
@@ -271,10 +279,10 @@ __device__ inline void mlp_forward_tile_keep(const DevCfg& c, const AT* Wbase, c
   }
 }
 
-template <int M, int NWAVES, typename AT>
+template <int M, int NWAVES, bool ORDERED, typename AT>
 __device__ inline void mlp_forward_tile(const DevCfg& c, const AT* Wbase, const float* scales, AT* act0, int ld0, AT* act1,
                                         int ld1, float* z, int ldz, Group<AT>& g) {
-  mlp_forward_tile_keep<M, NWAVES, AT>(c, Wbase, scales, act0, ld0, act1, ld1, z, ldz, g, [](int, int, int, f32x4) {});
+  mlp_forward_tile_keep<M, NWAVES, ORDERED, AT>(c, Wbase, scales, act0, ld0, act1, ld1, z, ldz, g, [](int, int, int, f32x4) {});
 }
 
 }  // namespace nbvh

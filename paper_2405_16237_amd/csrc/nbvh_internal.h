@@ -55,9 +55,11 @@ struct DevCfg {
 };
 
 // Auxiliary buffer: weight copies in the order the matrix-core tiles read
-// them (frag_index). Transposed copies for back-propagation, FP32 then BF16;
-// forward copies, BF16 then E4M3; then kFp8Floats floats: weight scales sw[k],
-// activation scales sa[k] (input of layer k), and the amax values they come from.
+// them (frag_index). Transposed copies for back-propagation, FP32 then BF16,
+// written by the optimiser and nbvh_sync_shadow; forward copies, BF16 (written
+// by each query from the shadow, order_weights) then E4M3 (by the calibration);
+// then kFp8Floats floats: weight scales sw[k], activation scales sa[k] (input of
+// layer k), and the amax values they come from.
 constexpr int kFp8Floats = 4 * kMaxLayers;
 __host__ __device__ inline uint64_t wt16_off(const DevCfg& c) { return c.n_wt * 4; }
 __host__ __device__ inline uint64_t wf16_off(const DevCfg& c) { return c.n_wt * 6; }

@@ -99,7 +99,8 @@ struct FragRun {
   int last;
 };
 
-// A layer's weights: N rows (output features) of K columns, K a multiple of 32.
+// A layer's weights: N rows (output features) of K columns, K a multiple of a
+// fragment's.
 template <typename AT, bool ORDERED>
 struct LayerW {
   static constexpr int FK = Mma<AT>::fk, E = FK / 4;

@@ -12,6 +12,13 @@
 
 #include "launch.h"
 
+namespace nbvh {
+struct SideStream {
+  hipStream_t stream;
+  hipEvent_t fork, join;
+};
+}  // namespace nbvh
+
 struct nbvh_ctx {
   nbvh_config cfg;
   nbvh::DevCfg dev;
@@ -24,10 +31,10 @@ struct nbvh_ctx {
   nbvh_tuning tune;
   bool fp8_ready;  // FP8 weights and scales in aux match the current parameters
   int tree_depth;  // inner levels of the N-BVH (traversal stack entries)
+  int device;      // the device the context was built on
   // a second stream of the context: the training step's weight-gradient GEMMs
   // run on it beside the table-gradient scatter (fork and join by events)
-  hipStream_t side;
-  hipEvent_t ev_fork, ev_join;
+  nbvh::SideStream side;
 };
 
 namespace nbvh {
@@ -220,9 +227,9 @@ static LaunchCtx make_launch(const nbvh_ctx* ctx, void* stream) {
   LaunchCtx L;
   memset(&L, 0, sizeof(L));
   L.stream = (hipStream_t)stream;
-  L.side = ctx->side;
-  L.ev_fork = ctx->ev_fork;
-  L.ev_join = ctx->ev_join;
+  L.side = ctx->side.stream;
+  L.ev_fork = ctx->side.fork;
+  L.ev_join = ctx->side.join;
   L.nodes = ctx->nodes;
   L.state = (DevState*)ctx->p.state_dev;
   L.cfg = ctx->dev;
@@ -296,6 +303,56 @@ constexpr size_t kNoAllocBytes = 64ull << 20;
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 constexpr int kMaxDevices = 64;
+
+// Second streams of destroyed contexts, for the contexts built next on their
+// device; a context has its stream and events to itself. They are handed on and
+// not destroyed: three test processes ended with a segmentation fault in a thread
+// of the runtime just after a context that had trained was destroyed together
+// with its stream and events, whose last completion that thread may still have
+// been handling. At most kSideIdle are kept on a device.
+constexpr int kSideIdle = 64;
+static std::mutex g_side_mu;
+static SideStream g_side_idle[kMaxDevices][kSideIdle];
+static int g_side_n[kMaxDevices];
+
+static void destroy_side(const SideStream& s) {
+  if (s.stream) (void)hipStreamDestroy(s.stream);
+  if (s.fork) (void)hipEventDestroy(s.fork);
+  if (s.join) (void)hipEventDestroy(s.join);
+}
+
+static bool take_side(int dev, SideStream* s) {
+  {
+    std::lock_guard<std::mutex> lock(g_side_mu);
+    if (dev >= 0 && dev < kMaxDevices && g_side_n[dev] > 0) {
+      *s = g_side_idle[dev][--g_side_n[dev]];
+      return true;
+    }
+  }
+  *s = SideStream{nullptr, nullptr, nullptr};
+  if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) == hipSuccess &&
+      hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) == hipSuccess &&
+      hipEventCreateWithFlags(&s->join, hipEventDisableTiming) == hipSuccess)
+    return true;
+  destroy_side(*s);
+  *s = SideStream{nullptr, nullptr, nullptr};
+  return false;
+}
+
+// waits for the stream's work, so that the caller may free the context's buffers
+static void give_side(int dev, const SideStream& s) {
+  if (!s.stream) return;
+  (void)hipStreamSynchronize(s.stream);
+  {
+    std::lock_guard<std::mutex> lock(g_side_mu);
+    if (dev >= 0 && dev < kMaxDevices && g_side_n[dev] < kSideIdle) {
+      g_side_idle[dev][g_side_n[dev]++] = s;
+      return;
+    }
+  }
+  destroy_side(s);
+}
+
 static std::mutex g_scratch_mu;
 static void* g_scratch_ptr[kMaxDevices];
 
@@ -415,9 +472,8 @@ nbvh_status nbvh_build(const nbvh_config* cfg, const float* leaf_boxes_host, uin
   ctx->n_cu = (hipGetDeviceProperties(&prop, dev) == hipSuccess) ? prop.multiProcessorCount : 256;
   if (ctx->n_cu <= 0) ctx->n_cu = 256;
   ctx->tune = nbvh_tuning{8, 0, 0, 8, 64, 0, 1, 8, 0, 0, 2, 0};
-  if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess ||
-      hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming) != hipSuccess) {
+  ctx->device = dev;
+  if (!take_side(dev, &ctx->side)) {
     set_error("creating the context's stream and events failed");
     nbvh_destroy(ctx);
     return NBVH_ERR_HIP;
@@ -976,12 +1032,7 @@ void nbvh_destroy(nbvh_ctx* ctx) {
     for (auto& e : ctx->prof->ev) hipEventDestroy(e);
     delete ctx->prof;
   }
-  if (ctx->side) {
-    (void)hipStreamSynchronize(ctx->side);
-    (void)hipStreamDestroy(ctx->side);
-  }
-  if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
-  if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
+  give_side(ctx->device, ctx->side);
   delete ctx;
 }
 

@@ -374,6 +374,7 @@ __device__ inline void query_direct(const DevCfg& c, const QueryJob& J, unsigned
       end = J.offsets[r + 1];
     }
   }
+  const uint32_t first = cur;
   const uint64_t mine = __ballot(ray != NBVH_MISS);
   if (mine == 0ull) return;
   const int last = 63 - __clzll((unsigned long long)mine);
@@ -406,7 +407,8 @@ __device__ inline void query_direct(const DevCfg& c, const QueryJob& J, unsigned
         const uint32_t leaf = s_leaf[m];
         const bool in = (leaf & NBVH_SEG_INSIDE) != 0u;
         const float t0 = sA[m].w, t1 = sB[m].w;
-        if (!((in ? -t1 : t0) < best_t)) {  // the segment starts at or after the best hit
+        // the segment starts at or after the best hit; a ray's first one is always evaluated
+        if (cur != first && !((in ? -t1 : t0) < best_t)) {
           more = false;
           break;
         }

@@ -122,3 +122,24 @@ def test_overflow_of_few_rays_is_flagged(lib, n):
     assert st["flags"] == 1 and st["last_n_segments"] == int(off[-1])
     assert (hits[~none] == 7.0).all()
     assert (hits[none].view(torch.int32)[:, 7] == -1).all() and (hits[none][:, :7] == 0).all()
+
+
+@pytest.mark.parametrize("n", [7, 300])
+def test_first_segment_at_infinity_counts_as_evaluated(lib, n):
+    """A ray without direction that begins at infinity crosses the leaves around
+    its origin there: its first segment is evaluated (no hit), its others not."""
+    b = np.array([[-1, -1, -1, 1, 1, 1], [-0.9, -0.9, -0.9, 0.9, 0.9, 0.9]], np.float32)
+    m = lib.NBVH(configs.C1_NET, b, np.full(3, -1.1, np.float32), 2.2)
+    m.set_params(configs.init_params(configs.C1_NET))
+    rays = _rays(n, 5)
+    rays[::3, 0:3] *= 0.2
+    rays[::3, 3], rays[::3, 4:7] = np.inf, 0.0
+    print("infinity", n, flush=True)
+    hits, counts = [], []
+    for wgs in (0, 1):
+        m.set_tuning(query_wgs_per_cu=wgs)
+        e = m.read_state()["n_evaluated"]
+        hits.append(m.query(rays, 2 * n).view(torch.int32))
+        counts.append(m.read_state()["n_evaluated"] - e)
+    assert torch.equal(hits[0], hits[1]) and (hits[0][::3, 7] == -1).all()
+    assert counts[0] == counts[1] >= (n + 2) // 3

@@ -596,8 +596,8 @@ static int query_per_cu(const LaunchCtx& L, size_t lds) {
 // the weights forward_layer reads, of a query or of the other calls
 static const void* mlp_weights(const LaunchCtx& L, bool query) {
   if (L.fp8) return (const char*)L.aux + fp8_weights_off(L.cfg);
-  if (L.precision == NBVH_FP32) return L.params;
-  return query ? (const void*)((const char*)L.aux + wf16_off(L.cfg)) : (const void*)L.params_lp;
+  if (L.precision == NBVH_FP32) return L.params + L.cfg.w_off[0];
+  return query ? (const char*)L.aux + wf16_off(L.cfg) : (const char*)L.params_lp + L.cfg.w_off[0] * 2;
 }
 
 // merge per-object hit records: closest t, ties to the lower object index
@@ -900,10 +900,10 @@ nbvh_status launch_calibrate_fp8(const LaunchCtx& L, const nbvh_probe* probes, u
   const void* table = L.params_lp;
   if (c.n_features == 2) {
     set_lds(k_calib_act<2>, lds);
-    k_calib_act<2><<<(n + kQM - 1) / kQM, 64 * kQWaves, lds, L.stream>>>(c, table, L.params, probes, n, f + 3 * kMaxLayers);
+    k_calib_act<2><<<(n + kQM - 1) / kQM, 64 * kQWaves, lds, L.stream>>>(c, table, L.params + c.w_off[0], probes, n, f + 3 * kMaxLayers);
   } else {
     set_lds(k_calib_act<4>, lds);
-    k_calib_act<4><<<(n + kQM - 1) / kQM, 64 * kQWaves, lds, L.stream>>>(c, table, L.params, probes, n, f + 3 * kMaxLayers);
+    k_calib_act<4><<<(n + kQM - 1) / kQM, 64 * kQWaves, lds, L.stream>>>(c, table, L.params + c.w_off[0], probes, n, f + 3 * kMaxLayers);
   }
   k_fp8_scales<<<1, 64, 0, L.stream>>>(c, f);
   k_quantize_weights<<<dim3(64, c.hidden + 1), 256, 0, L.stream>>>(c, L.params, f, w8);

@@ -90,22 +90,23 @@ struct Mma<float> {
   }
 };
 
-// Where a wave finds four consecutive fragments of a row tile: a uniform base,
-// the lane's byte offset and how many of the four the layer has (the last one
-// stands in for the others, which are not used).
+// Where a wave finds four consecutive fragments of a row tile: the lane's byte
+// offset into the weights and which of the four is the layer's last.
 struct FragRun {
-  const char* base;
-  uint32_t lane_off;
+  uint32_t off;
   int last;
 };
 
 // A layer's weights: N rows (output features) of K columns, K a multiple of a
-// fragment's.
+// fragment's. All layers are read from one base and 32-bit offsets: a pointer of
+// its own for each kept so many scalar registers that the query moved them out
+// and in (69 in the frame query's kernel, 54 now).
 template <typename AT, bool ORDERED>
 struct LayerW {
   static constexpr int FK = Mma<AT>::fk, E = FK / 4;
   static constexpr int stride = ORDERED ? 64 * E * (int)sizeof(AT) : FK * (int)sizeof(AT);  // between fragments
-  const AT* p;  // in fragment order if ORDERED, else row-major
+  const AT* p;   // the first layer's, in fragment order if ORDERED, else row-major
+  uint32_t off;  // bytes from there to this layer's
   int K, N;
   __device__ int tiles() const { return (N + 15) >> 4; }
   __device__ FragRun run(int nt, int kf) const {
@@ -113,18 +114,15 @@ struct LayerW {
     FragRun r;
     r.last = nkf - 1 - kf;
     if constexpr (ORDERED) {
-      r.base = (const char*)p + ((size_t)nt * nkf + kf) * stride;
-      r.lane_off = (uint32_t)lane * (E * (int)sizeof(AT));
+      r.off = off + (uint32_t)(nt * nkf + kf) * stride + (uint32_t)lane * (E * (int)sizeof(AT));
     } else {
       const int n = min(nt * 16 + (lane & 15), N - 1);  // rows past the last repeat it: outputs nobody reads
-      r.base = (const char*)p + (size_t)kf * stride;
-      r.lane_off = (uint32_t)(n * K + E * (lane >> 4)) * (uint32_t)sizeof(AT);
+      r.off = off + (uint32_t)(n * K + E * (lane >> 4)) * (uint32_t)sizeof(AT) + (uint32_t)kf * stride;
     }
     return r;
   }
-  __device__ static typename Mma<AT>::Frag load(const FragRun& r, int i) {
-    const char NBVH_GLOBAL* b = (const char NBVH_GLOBAL*)r.base + min(i, r.last) * stride;
-    return *(const typename Mma<AT>::Frag NBVH_GLOBAL*)(b + r.lane_off);
+  __device__ typename Mma<AT>::Frag load(const FragRun& r, int i) const {
+    return *(const typename Mma<AT>::Frag NBVH_GLOBAL*)((const char NBVH_GLOBAL*)p + (r.off + (uint32_t)(i * stride)));
   }
 };
 
@@ -134,13 +132,17 @@ struct Group {
   typename Mma<AT>::Frag a[4];
 };
 
-// the wave's first group of a layer
+// the wave's first group of a layer, as far as it has one
 template <typename AT, bool ORDERED>
 __device__ inline Group<AT> first_group(const LayerW<AT, ORDERED>& w) {
   Group<AT> g;
-  const FragRun r = w.run(min(wave_id(), w.tiles() - 1), 0);
+  const int wave = wave_id();
+  if (wave < w.tiles()) {
+    const FragRun r = w.run(wave, 0);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) g.a[i] = w.load(r, i);
+    for (int i = 0; i < 4; ++i)
+      if (i <= r.last) g.a[i] = w.load(r, i);
+  }
   return g;
 }
 
@@ -148,7 +150,9 @@ __device__ inline Group<AT> first_group(const LayerW<AT, ORDERED>& w) {
 // holds the wave's first group on entry and, given `next`, that layer's on
 // return. A fragment's registers are loaded again as soon as its products are
 // issued, so the next group (of this column tile, the next one or the next
-// layer) travels meanwhile with no copies, which would wait for it.
+// layer) travels meanwhile with no copies, which would wait for it. Fragments
+// past a layer's last are neither loaded nor multiplied: with 64 columns, two of
+// a group's four (10^6 camera rays, MLP 64-3x64-5: 480 us with all loaded, 463).
 template <int M, int NWAVES, typename AT, bool ORDERED, typename Epi>
 __device__ inline void gemm_tile(const AT* act_in, int ld_in, const LayerW<AT, ORDERED>& w, Group<AT>& g, Epi epi,
                                  const LayerW<AT, ORDERED>* next = nullptr) {
@@ -165,19 +169,19 @@ __device__ inline void gemm_tile(const AT* act_in, int ld_in, const LayerW<AT, O
     for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int kf = 0; kf < nkf; kf += 4) {
       const bool here = kf + 4 < nkf || nt + NWAVES < n_tiles;
-      FragRun r{};
+      FragRun r{0u, -1};
       if (here) r = kf + 4 < nkf ? w.run(nt, kf + 4) : w.run(nt + NWAVES, 0);
       else if (more) r = next->run(wave, 0);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        if (kf + i < nkf) {
+        if (i == 0 || kf + i < nkf) {
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) {
             const Frag b = lds_load<Frag>(arow + (size_t)mt * 16 * ld_in + (kf + i) * FK);
             acc[mt] = Mma<AT>::mul(g.a[i], b, acc[mt]);
           }
         }
-        if (here || more) g.a[i] = w.load(r, i);
+        if (i <= r.last) g.a[i] = w.load(r, i);
       }
     }
 #pragma unroll
@@ -186,7 +190,8 @@ __device__ inline void gemm_tile(const AT* act_in, int ld_in, const LayerW<AT, O
   if (wave >= n_tiles && more) {
     const FragRun r = next->run(wave, 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) g.a[i] = w.load(r, i);
+    for (int i = 0; i < 4; ++i)
+      if (i <= r.last) g.a[i] = w.load(r, i);
   }
 }
 
@@ -222,10 +227,11 @@ constexpr bool kOrderedQuery = sizeof(AT) < 4;
 template <typename AT>
 constexpr bool kOrderedForward = sizeof(AT) == 1;
 
-// weights of layer k
+// weights of layer k; base: the first layer's
 template <bool ORDERED, typename AT>
 __device__ inline LayerW<AT, ORDERED> forward_layer(const DevCfg& c, const AT* base, int k) {
-  return LayerW<AT, ORDERED>{base + (ORDERED ? c.wf_off[k] : c.w_off[k]), c.fan_in[k], c.fan_out[k]};
+  const uint64_t off = ORDERED ? c.wf_off[k] : c.w_off[k] - c.w_off[0];
+  return LayerW<AT, ORDERED>{base, (uint32_t)off * (uint32_t)sizeof(AT), c.fan_in[k], c.fan_out[k]};
 }
 
 // Full forward of the tile: act0 holds the encoded input [M][n_in]; hidden

@@ -243,14 +243,17 @@ __device__ inline void encode_tile(const DevCfg& c, const void* table, const flo
       float wx[U], wy[U], wz[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int l = act[u] ? lg + u * NWAVES : 0;
+        // a group's missing levels are skipped (eight levels on eight waves have
+        // one a wave: 10^6 camera rays, small network, 465 -> 439 us)
+        if (!act[u]) continue;
+        const int l = lg + u * NWAVES;
         const int N = c.level_res[l];
         const bool dense = (c.dense_mask >> l) & 1u;
         int cx, cy, cz;
         cell_weight(x[0], N, cx, wx[u]);
         cell_weight(x[1], N, cy, wy[u]);
         cell_weight(x[2], N, cz, wz[u]);
-        const bool need = act[u] && valid && (cx != pcx[u] || cy != pcy[u] || cz != pcz[u]);
+        const bool need = valid && (cx != pcx[u] || cy != pcy[u] || cz != pcz[u]);
         pcx[u] = cx;
         pcy[u] = cy;
         pcz[u] = cz;

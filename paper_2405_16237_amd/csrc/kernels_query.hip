@@ -240,8 +240,14 @@ __device__ inline void query_eval_loop(const DevCfg& c, const QueryJob& J, unsig
       const uint32_t c1 = s_cur[lane] + 1;
       if (c1 < s_end[lane]) nxt = J.segs[c1];
     }
-    // the first weights travel while the table is gathered
-    Group<AT> g = first_group(forward_layer<kOrderedQuery<AT>>(c, (const AT*)J.W, 0));
+    // The first weights travel while the table is gathered, with 4-byte entries.
+    // Wider ones leave no registers for that under the bound of four waves a
+    // SIMD: the kernels spilled up to 64 (10^6 camera rays, four features: FP32
+    // MLP 64-3x64-8 530 us so, 500 with the weights after the gathers; 256-4x256-8
+    // in BF16 945 and 923).
+    constexpr bool kEarly = F * (LP ? 2 : 4) == 4;
+    Group<AT> g;
+    if constexpr (kEarly) g = first_group(forward_layer<kOrderedQuery<AT>>(c, (const AT*)J.W, 0));
     const float qscale = sizeof(AT) == 1 ? J.scales[kMaxLayers] : 1.0f;
     if (!kTail || rows > 32)
       encode_tile<AT, F, LP, NW, U, PR>(c, J.table, sA, sB, pos, s_valid, act0, ld0, qscale, ltab, J.lds_levels);
@@ -249,6 +255,7 @@ __device__ inline void query_eval_loop(const DevCfg& c, const QueryJob& J, unsig
       if (rows > 16) encode_rows<AT, F, LP, NW, 32>(c, J.table, sA, sB, rows, act0, ld0, qscale);
       else encode_rows<AT, F, LP, NW, 16>(c, J.table, sA, sB, rows, act0, ld0, qscale);
     }
+    if constexpr (!kEarly) g = first_group(forward_layer<kOrderedQuery<AT>>(c, (const AT*)J.W, 0));
     __syncthreads();
     if constexpr (sizeof(AT) > 1) {
       if (J.u_trace) {  // uniform over the launch: the feature tile as the MLP reads it

@@ -405,8 +405,11 @@ constexpr uint32_t kStage = 16;
 // With few rays the walk's time is its chain of node loads (about 1 us a visit
 // from L2), so the whole tree, if it has at most kTreeNodes nodes, is first
 // copied to LDS; with many rays other waves hide that latency and the copy
-// would cost occupancy instead.
-constexpr uint32_t kTreeNodes = 1023, kTreeRays = 16384;
+// would cost occupancy instead. A tree of up to kTreeSmall nodes (8 KiB) costs
+// none, and spares many rays the walk's wait for the L1: 64 leaves, camera rays,
+// 65,536 41 us from memory and 35 from LDS, 10^6 68 and 56; 300,000 random rays
+// 74 and 58.
+constexpr uint32_t kTreeNodes = 1023, kTreeRays = 16384, kTreeSmall = 127;
 template <bool TREE>
 __device__ inline const Node* copy_tree(const Node* __restrict__ nodes, uint32_t n_nodes, void* lds) {
   if constexpr (TREE) {
@@ -1431,7 +1434,7 @@ nbvh_status launch_traverse(const LaunchCtx& L, const nbvh_ray* rays, uint32_t n
   const uint32_t grid = ray_blocks(n_rays);
   const WeightCopy wc = active ? weight_copy(L) : WeightCopy{nullptr, nullptr, 0};  // a query follows
   const uint32_t stack_words = 256u * (uint32_t)(L.stack_depth > 0 ? L.stack_depth : 1);
-  const bool in_lds = n_rays <= kTreeRays && L.n_nodes <= kTreeNodes && L.tune.traverse_mode != 1;
+  const bool in_lds = L.n_nodes <= (n_rays <= kTreeRays ? kTreeNodes : kTreeSmall) && L.tune.traverse_mode != 1;
   const size_t lds = (size_t)stack_words * 4 + (in_lds ? (size_t)L.n_nodes * sizeof(Node) : 0);
   if (active && !order && n_rays > 0 && n_rays <= kOneRays) {
     auto kern = L.cfg.inside_reverse ? (in_lds ? k_traverse_one<true, true> : k_traverse_one<true, false>)

@@ -37,7 +37,7 @@ def _rays(n, kind):
 
 
 @pytest.mark.parametrize("kind", ["equal", "one apart", "mostly missing", "random"])
-@pytest.mark.parametrize("leaves", [64, 2000])
+@pytest.mark.parametrize("leaves", [64, 128, 129, 2000])
 @pytest.mark.parametrize("inside", ["clip", "reverse"])
 def test_walks_of_lanes_and_waves_agree(lib, leaves, kind, inside):
     rng = np.random.default_rng(leaves)

@@ -236,7 +236,9 @@ __device__ inline void walk_wave(const Node* __restrict__ nodes, const RayPre& R
     bool ia = false, ib = false;
     const bool h0 = live && slab<REV>(R, lo0, hi0, a0, a1, ia);
     const bool h1 = live && (c1 != kEmptyChild) && slab<REV>(R, lo1, hi1, b0, b1, ib);
-    emit_leaves(h0 && c0 < 0, c0, a0, a1, ia, h1 && c1 < 0, c1, b0, b1, ib, emit);
+    // (half the nodes have no leaf below them: 300,000 random rays, 16,384 leaves,
+    // wave walks only, 1,940 us without the test, 1,843 with it, camera rays 373 and 354)
+    if (c0 < 0 || c1 < 0) emit_leaves(h0 && c0 < 0, c0, a0, a1, ia, h1 && c1 < 0, c1, b0, b1, ib, emit);
     const bool e0 = c0 >= 0 && __ballot(h0) != 0ull;
     const bool e1 = c1 >= 0 && c1 != kEmptyChild && __ballot(h1) != 0ull;
     int32_t next;

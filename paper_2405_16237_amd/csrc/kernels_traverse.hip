@@ -132,7 +132,7 @@ __device__ inline void quad_load_nodes(const Node* __restrict__ nodes, int32_t n
 // it needs as many entries as the tree has inner levels. Called by every lane
 // of the wave together; lanes with live = false emit nothing. TREE: `tree` is
 // the workgroup's LDS copy of the nodes, which is read instead.
-template <bool REV, bool TREE, typename Emit>
+template <bool REV, bool TREE, bool MIXED, typename Emit>
 __device__ inline void walk(const Node* __restrict__ nodes, const Node* tree, const RayPre& R, bool live, Emit emit,
                             int32_t* stk, uint32_t stride) {
   int sp = 0;
@@ -144,8 +144,9 @@ __device__ inline void walk(const Node* __restrict__ nodes, const Node* tree, co
     // lane reads its own node, one line a quad as well, and the transpose is spared:
     // 10^6 camera rays over 64 leaves 79 -> 69 us, one ray over 16,384 leaves 33 -> 28,
     // and as incoherent waves thin out: 3,000 random rays over 16,384 leaves 224 -> 195.
-    bool apart = false;
-    if constexpr (!TREE) {
+    // Rays known to be scattered (MIXED false: a selection) pay 5 % for the choice.
+    bool apart = true;
+    if constexpr (MIXED && !TREE) {
       uint32_t lo = live ? (uint32_t)node : 0xffffffffu, hi = live ? (uint32_t)node : 0u;
       lo = min(lo, quad_swap(lo, 1));
       hi = max(hi, quad_swap(hi, 1));
@@ -314,14 +315,14 @@ __device__ inline bool wave_walks(int mode, const Node* __restrict__ nodes, cons
 
 // The walk the mode asks for. Called by every lane of the wave (the
 // wave-coherent walk needs them all); lanes with live = false emit nothing.
-template <bool REV, bool TREE = false, typename Emit>
+template <bool REV, bool TREE = false, bool MIXED = true, typename Emit>
 __device__ inline void walk_mode(int mode, const Node* __restrict__ nodes, const RayPre& R, bool live, Emit emit,
                                  int32_t* stk, uint32_t stride, const Node* tree = nullptr) {
   float g[3] = {0.f, 0.f, 0.f};
   if (wave_walks(mode, nodes, R, live, g))
     walk_wave<REV>(nodes, R, live, emit, g[0], g[1], g[2]);
   else
-    walk<REV, TREE>(nodes, tree, R, live, emit, stk, stride);
+    walk<REV, TREE, MIXED>(nodes, tree, R, live, emit, stk, stride);
 }
 
 // The last record of a sorted run, kept in registers: a segment that sorts
@@ -554,7 +555,7 @@ __global__ __launch_bounds__(256) void k_first_hits(const Node* __restrict__ nod
     int32_t best = -1;
     float b0 = 0.f, b1 = 0.f;
     const RayPre R = load_ray_or_none(rays, r, live);
-    walk_mode<REV>(
+    walk_mode<REV, false, false>(
         mode, nodes, R, live,
         [&](int32_t leaf, float t0, float t1, bool inside) {
           if (HIST)

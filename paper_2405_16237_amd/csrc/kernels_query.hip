@@ -546,9 +546,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
   __syncthreads();
   Group<AT> g = first_group(forward_layer<kOrderedForward<AT>>(c, (const AT*)W, 0));
-  encode_tile<AT, F, LP, kQWaves>(c, table, sA, sB, pos, s_valid, act0, ld0, sizeof(AT) == 1 ? scales[kMaxLayers] : 1.0f);
-  __syncthreads();
-  mlp_forward_tile<kQM, kQWaves, kOrderedForward<AT>, AT>(c, (const AT*)W, scales, act0, ld0, act1, ld1, z, kOutPad, g);
+  const float qscale = sizeof(AT) == 1 ? scales[kMaxLayers] : 1.0f;
+  // A last tile of up to 32 probes is a tile of 32 or 16 rows, as at the end of a
+  // query: what counts there is the chain of one wave's gathers and layers (one
+  // probe, frame network: 20 us on 64 rows, 13 on 16).
+  const uint32_t rows = min((uint32_t)kQM, n - base);
+  if (rows > 32) {
+    encode_tile<AT, F, LP, kQWaves>(c, table, sA, sB, pos, s_valid, act0, ld0, qscale);
+    __syncthreads();
+    mlp_forward_tile<kQM, kQWaves, kOrderedForward<AT>, AT>(c, (const AT*)W, scales, act0, ld0, act1, ld1, z, kOutPad, g);
+  } else if (rows > 16) {
+    encode_rows<AT, F, LP, kQWaves, 32>(c, table, sA, sB, (int)rows, act0, ld0, qscale);
+    __syncthreads();
+    mlp_forward_tile<32, kQWaves, kOrderedForward<AT>, AT>(c, (const AT*)W, scales, act0, ld0, act1, ld1, z, kOutPad, g);
+  } else {
+    encode_rows<AT, F, LP, kQWaves, 16>(c, table, sA, sB, (int)rows, act0, ld0, qscale);
+    __syncthreads();
+    mlp_forward_tile<16, kQWaves, kOrderedForward<AT>, AT>(c, (const AT*)W, scales, act0, ld0, act1, ld1, z, kOutPad, g);
+  }
   for (int e = threadIdx.x; e < kQM * c.n_out; e += blockDim.x) {
     const int m = e / c.n_out, o = e - m * c.n_out;
     if (base + m < n) zout[(size_t)(base + m) * c.n_out + o] = z[m * kOutPad + o];

@@ -194,14 +194,19 @@ typedef struct {
 typedef struct nbvh_ctx nbvh_ctx; /* opaque host handle */
 
 /* Launch-shape knobs (defaults shown). Results do not depend on them beyond
- * floating-point summation order; an autotuner may search them. Changing
- * wgrad_splits, scatter_lds_kb, scatter_binned or scatter_hash_levels changes
- * nbvh_workspace_bytes. */
+ * floating-point summation order; an autotuner may search them. Two ways of
+ * evaluating belong to the default shape of a query (query_waves 8, two levels
+ * unrolled, query_pairs 0, nothing staged by query_lds_kb): tiles of fewer rows
+ * once the ray queue is empty and, with query_wgs_per_cu 0 too, all segments of
+ * up to 16,384 rays at once. Any other setting takes every ray's segments one
+ * after the other in full tiles. Changing wgrad_splits, scatter_lds_kb,
+ * scatter_binned or scatter_hash_levels changes nbvh_workspace_bytes. */
 typedef struct {
   int32_t query_waves;      /* waves per query workgroup: 4 or 8 (8) */
   int32_t query_unroll;     /* (sample, level) pairs gathered together: 2, 3, 4; 0 = 2, or 3 with pair
                                loads of 4-byte entries (0) */
-  int32_t query_wgs_per_cu; /* persistent query workgroups per compute unit; 0 = as many as LDS allows (0) */
+  int32_t query_wgs_per_cu; /* persistent query workgroups per compute unit; 0 = as many as LDS allows, and
+                               few rays' segments all at once (0) */
   int32_t train_waves;      /* waves per training-tile workgroup: 4 or 8 (8) */
   int32_t wgrad_splits;     /* batch splits of the weight-gradient GEMMs: 1..256 (64) */
   int32_t scatter_lds_kb;   /* LDS budget for coarse dense levels held whole per compute unit in the

@@ -623,8 +623,8 @@ nbvh_status launch_first_hits(const LaunchCtx& L, const nbvh_ray* rays, uint32_t
 }
 
 // ---------------------------------------------------------------------------
-// exclusive scan of uint32 counts (3 kernels: tile scan, scan of tile sums,
-// add). Tile = 256 threads x 4 items.
+// exclusive scan of uint32 counts: tile scan, then add (beyond kScanDirectTiles
+// tiles a scan of the tile sums in between). Tile = 256 threads x 4 items.
 // ---------------------------------------------------------------------------
 constexpr int kScanItems = 4;
 constexpr int kScanTile = 256 * kScanItems;
@@ -731,9 +731,8 @@ __global__ __launch_bounds__(256) void k_scan_add(uint32_t* __restrict__ out, ui
 }
 
 // The traversal's two scans at once: segment offsets of the counts and, for
-// the active-ray list, positions among the rays with a segment (tile scans,
-// one block per scan of the tile sums, add; the totals go to total_seg and
-// total_ray).
+// the active-ray list, positions among the rays with a segment (tile scans, add;
+// beyond kScanDirectTiles tiles one block each scans the tile sums in between).
 // (positions follow the ray order `perm` when one is given: pos[i] is the
 // place of ray perm[i])
 __global__ __launch_bounds__(256) void k_scan2_tiles(const uint32_t* __restrict__ in, uint32_t n,
